@@ -114,8 +114,8 @@ int mfq_space_random(const mfq_space* space, int precision, void* x, uint64_t se
  * point in `precision` and 1D tables of the map's sines and cosines.  The merged tensor G_q = w_q
  * a(x_q) det(J_q) J_q^{-1} J_q^{-T} follows from them exactly: the map's Jacobian is I + 1 g^T with g
  * a product of 1D functions, so G_q = c_q (D^2 I - D (1 g^T + g 1^T) + |g|^2 1 1^T), D = 1 + g1 + g2
- * + g3, c_q = w_q a(x_q) h / D (evaluated in FP64, rounded once).  MFQ_FP32_MFMA operators store
- * the six values of G_q as well.  On deformed meshes the reported size is that of six values per
+ * + g3, c_q = w_q a(x_q) h / D (evaluated in FP64, rounded once); g and D are held and applied in FP64.
+ * MFQ_FP32_MFMA operators store the six values of G_q as well.  On deformed meshes the reported size is that of six values per
  * point, of which the first sixth is used. */
 int mfq_op_create(const mfq_space* space, double alpha, int precision, mfq_op** out);
 void mfq_op_destroy(mfq_op* op);

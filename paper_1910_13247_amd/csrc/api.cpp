@@ -132,7 +132,7 @@ int mfq_op_create(const mfq_space* space, double alpha, int precision, mfq_op** 
   // one value per quadrature point and the 1D tables.  On deformed meshes the reported size keeps
   // the room of six values per point (callers hold buffers of that size); the rest is unused.
   const size_t rs = real_size(precision), points = nb * (p + 1) * lanes;
-  const size_t scal = round_up(points * rs, 256) + round_up(4 * (size_t)space->mesh->n * (p + 1) * rs, 256);
+  const size_t scal = round_up(points * rs, 256) + round_up(4 * (size_t)space->mesh->n * (p + 1) * sizeof(double), 256);
   const size_t six = round_up(6 * points * rs, 256);
   op->full_bytes = op->mfma ? six : 0;
   op->geo_bytes = space->mesh->amplitude != 0.0 && !op->mfma ? std::max(six, scal) : scal;

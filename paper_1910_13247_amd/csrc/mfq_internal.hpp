@@ -171,7 +171,7 @@ struct mfq_op {
   // G_q = c_q (D^2 I - D (1 g^T + g 1^T) + |g|^2 1 1^T): c_q stored, g and D from 1D tables (geo_bytes
   // covers both)
   void* scal = nullptr;       // [n_bricks][p+1][lanes] of the precision's type
-  void* tab = nullptr;        // [2][n (p+1)][2]: (sin, cos)(pi X) along X1, and along X2 and X3
+  void* tab = nullptr;        // double [2][n (p+1)][2]: (sin, cos)(pi X) along X1, and along X2 and X3
   void* full = nullptr;       // matrix-core operators: [n_bricks][p+1][3][lanes][2], the whole G_q
 };
 
