@@ -132,7 +132,7 @@ int mfq_op_create(const mfq_space* space, double alpha, int precision, mfq_op** 
   // one value per quadrature point and the 1D tables.  On deformed meshes the reported size keeps
   // the room of six values per point (callers hold buffers of that size); the rest is unused.
   const size_t rs = real_size(precision), points = nb * (p + 1) * lanes;
-  const size_t scal = round_up(points * rs, 256) + round_up(4 * (size_t)space->mesh->n * (p + 1) * sizeof(double), 256);
+  const size_t scal = round_up(points * rs, 256) + round_up(8 * (size_t)space->mesh->n * (p + 1) * sizeof(double), 256);
   const size_t six = round_up(6 * points * rs, 256);
   op->full_bytes = op->mfma ? six : 0;
   op->geo_bytes = space->mesh->amplitude != 0.0 && !op->mfma ? std::max(six, scal) : scal;
@@ -176,8 +176,7 @@ int mfq_op_bind(mfq_op* op, void* dev_buf, size_t bytes, void* hip_stream) {
                                            lanes_per_brick(op->space->p) * real_size(op->precision), 256);
   op->full = op->full_bytes ? (char*)op->scal + op->geo_bytes : nullptr;
   const OpView v = view(op);
-  hipError_t e = launch_fill_index(v, op->idx, st);
-  if (e == hipSuccess) e = launch_geometry(v, op->precision, op->scal, op->tab, op->full, st);
+  const hipError_t e = launch_setup(v, op->precision, op->idx, op->tab, op->scal, op->full, st);
   if (e != hipSuccess) {
     op->buf = nullptr;
     return fail(MFQ_EHIP, "operator setup launch failed: %s", hipGetErrorString(e));

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kCsrBlock) void csr_values_kernel(const double* __r
     const int t = q / T, e = q - t * T;
     const Real2<double> x = tab[ci * N1 + e % N1], y = tab[(n + cj) * N1 + e / N1], z = tab[(n + ck) * N1 + t];
     double G[6];
-    point_tensor(PointMap{{x.x, y.x, z.x}, {x.y, y.y, z.y}}, amp, cp[t * NT + e], G);
+    point_tensor(PointMap{{x, y, z}, {}}, amp, cp[t * NT + e], G);
 #pragma unroll
     for (int m = 0; m < 6; ++m) Gs[m][q] = G[m];
   }

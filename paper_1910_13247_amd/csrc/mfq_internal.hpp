@@ -171,7 +171,7 @@ struct mfq_op {
   // G_q = c_q (D^2 I - D (1 g^T + g 1^T) + |g|^2 1 1^T): c_q stored, g and D from 1D tables (geo_bytes
   // covers both)
   void* scal = nullptr;       // [n_bricks][p+1][lanes] of the precision's type
-  void* tab = nullptr;        // double [2][n (p+1)][2]: (sin, cos)(pi X) along X1, and along X2 and X3
+  void* tab = nullptr;        // double [4][n (p+1)][2]: (sin, cos) of pi X and of 2 pi X along X1, and along X2 and X3
   void* full = nullptr;       // matrix-core operators: [n_bricks][p+1][3][lanes][2], the whole G_q
 };
 
@@ -249,9 +249,8 @@ int64_t own_groups(int p, int shape, int n);
 int own_shape(int p, int precision, int64_t small_groups, int64_t large_groups);
 
 // ---------------------------------------------------------------- launchers (kernels_*.hip)
-hipError_t launch_fill_index(const OpView& v, int* idx, hipStream_t st);
-// the operator's scalars and 1D tables (and with `full` the whole tensors)
-hipError_t launch_geometry(const OpView& v, int precision, void* scal, void* tab, void* full, hipStream_t st);
+// the operator's data: index lattices, 1D tables, scalars (and with `full` the whole tensors)
+hipError_t launch_setup(const OpView& v, int precision, int* idx, void* tab, void* scal, void* full, hipStream_t st);
 hipError_t launch_geometry_export(const OpView& v, int precision, double* out, hipStream_t st);
 // dst = A src (accumulate = false: every node written, no clearing needed) or dst += A src.
 hipError_t launch_vmult_cells(const OpView& v, int precision, const void* src, void* dst, bool accumulate,
