@@ -129,13 +129,19 @@ int mfq_op_create(const mfq_space* space, double alpha, int precision, mfq_op** 
   const size_t nb = (size_t)op->bricks.n_bricks;
   const size_t lanes = (size_t)lanes_per_brick(p);
   op->idx_bytes = round_up(nb * (size_t)lattice_per_brick(p) * sizeof(int), 256);
-  // one value per quadrature point and the 1D tables.  On deformed meshes the reported size keeps
-  // the room of six values per point (callers hold buffers of that size); the rest is unused.
+  // one value per quadrature point and the 1D tables; FP32 operators on deformed meshes also the values
+  // in FP64.  On deformed meshes the reported size keeps the room of six values per point (callers
+  // hold buffers of that size); the rest is unused.
   const size_t rs = real_size(precision), points = nb * (p + 1) * lanes;
-  const size_t scal = round_up(points * rs, 256) + round_up(8 * (size_t)space->mesh->n * (p + 1) * sizeof(double), 256);
+  const bool curved = space->mesh->amplitude != 0.0;
+  op->scal_bytes = round_up(points * rs, 256);
+  op->tab_bytes = round_up(8 * (size_t)space->mesh->n * (p + 1) * sizeof(double), 256);
+  const size_t c64 = curved && op->precision == MFQ_FP32 && !op->mfma ? points * sizeof(double) : 0;
+  const size_t used = op->scal_bytes + op->tab_bytes + round_up(c64, 256);
   const size_t six = round_up(6 * points * rs, 256);
+  op->has_c64 = c64 != 0;
   op->full_bytes = op->mfma ? six : 0;
-  op->geo_bytes = space->mesh->amplitude != 0.0 && !op->mfma ? std::max(six, scal) : scal;
+  op->geo_bytes = curved && !op->mfma ? std::max(six, used) : used;
   *out = op;
   return MFQ_OK;
 }
@@ -172,11 +178,11 @@ int mfq_op_bind(mfq_op* op, void* dev_buf, size_t bytes, void* hip_stream) {
   op->buf = dev_buf;
   op->idx = (int*)dev_buf;
   op->scal = (char*)dev_buf + op->idx_bytes;
-  op->tab = (char*)op->scal + round_up((size_t)op->bricks.n_bricks * (op->space->p + 1) *
-                                           lanes_per_brick(op->space->p) * real_size(op->precision), 256);
+  op->tab = (char*)op->scal + op->scal_bytes;
+  op->c64 = op->has_c64 ? (double*)((char*)op->tab + op->tab_bytes) : nullptr;
   op->full = op->full_bytes ? (char*)op->scal + op->geo_bytes : nullptr;
   const OpView v = view(op);
-  const hipError_t e = launch_setup(v, op->precision, op->idx, op->tab, op->scal, op->full, st);
+  const hipError_t e = launch_setup(v, op->precision, op->idx, op->tab, op->scal, op->c64, op->full, st);
   if (e != hipSuccess) {
     op->buf = nullptr;
     return fail(MFQ_EHIP, "operator setup launch failed: %s", hipGetErrorString(e));

@@ -164,14 +164,15 @@ struct mfq_op {
   bool mfma = false;          // FP32 cell loop on the matrix cores (created as MFQ_FP32_MFMA)
   bool fuse = MFQ_FUSE_DEFAULT != 0;  // vector updates fused into the cell loop (mfq_op_set_fused_updates)
   mfq::Bricks bricks;
-  size_t idx_bytes, geo_bytes, full_bytes;
+  size_t idx_bytes, scal_bytes, tab_bytes, geo_bytes, full_bytes;  // geo_bytes covers scal, tab and c64
+  bool has_c64 = false;
   void* buf = nullptr;        // caller-owned device memory
   int* idx = nullptr;         // [n_bricks][lattice]: global node of each brick-lattice node,
                               // ~g on Dirichlet nodes, INT_MIN outside the mesh
-  // G_q = c_q (D^2 I - D (1 g^T + g 1^T) + |g|^2 1 1^T): c_q stored, g and D from 1D tables (geo_bytes
-  // covers both)
+  // G_q = c_q (D^2 I - D (1 g^T + g 1^T) + |g|^2 1 1^T): c_q stored, g and D from 1D tables
   void* scal = nullptr;       // [n_bricks][p+1][lanes] of the precision's type
   void* tab = nullptr;        // double [4][n (p+1)][2]: (sin, cos) of pi X and of 2 pi X along X1, and along X2 and X3
+  double* c64 = nullptr;      // FP32 on deformed meshes: c_q before rounding (set-up's diagonal)
   void* full = nullptr;       // matrix-core operators: [n_bricks][p+1][3][lanes][2], the whole G_q
 };
 
@@ -217,6 +218,7 @@ struct OpView {
   const int* idx;
   const void* scal;
   const void* tab;
+  const double* c64;
   const void* full;
   bool mfma;
   double x0;                  // X1 offset of the mesh
@@ -230,7 +232,7 @@ inline OpView view(const mfq_op* op) {
   const mfq_space* s = op->space;
   const int faces = s->bc_faces >= 0 ? s->bc_faces : (s->bc ? 0b111111 : 0);
   return OpView{s->p, s->mesh->n, s->bc, s->n_cells, s->n_dofs, s->mesh->amplitude, op->alpha, op->bricks,
-                op->idx, op->scal, op->tab, op->full, op->mfma, s->mesh->x0, faces, s->side ? (int)s->n_dofs : -1,
+                op->idx, op->scal, op->tab, op->c64, op->full, op->mfma, s->mesh->x0, faces, s->side ? (int)s->n_dofs : -1,
                 nullptr, nullptr};
 }
 
@@ -250,7 +252,8 @@ int own_shape(int p, int precision, int64_t small_groups, int64_t large_groups);
 
 // ---------------------------------------------------------------- launchers (kernels_*.hip)
 // the operator's data: index lattices, 1D tables, scalars (and with `full` the whole tensors)
-hipError_t launch_setup(const OpView& v, int precision, int* idx, void* tab, void* scal, void* full, hipStream_t st);
+hipError_t launch_setup(const OpView& v, int precision, int* idx, void* tab, void* scal, double* c64, void* full,
+                        hipStream_t st);
 hipError_t launch_geometry_export(const OpView& v, int precision, double* out, hipStream_t st);
 // dst = A src (accumulate = false: every node written, no clearing needed) or dst += A src.
 hipError_t launch_vmult_cells(const OpView& v, int precision, const void* src, void* dst, bool accumulate,
