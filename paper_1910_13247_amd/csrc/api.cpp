@@ -131,17 +131,18 @@ int mfq_op_create(const mfq_space* space, double alpha, int precision, mfq_op** 
   op->idx_bytes = round_up(nb * (size_t)lattice_per_brick(p) * sizeof(int), 256);
   // one value per quadrature point and the 1D tables; FP32 operators on deformed meshes also the values
   // in FP64.  On deformed meshes the reported size keeps the room of six values per point (callers
-  // hold buffers of that size); the rest is unused.
-  const size_t rs = real_size(precision), points = nb * (p + 1) * lanes;
+  // hold buffers of that size); the rest is unused.  Matrix-core operators hold the six values alone.
+  const size_t rs = real_size(precision), points = nb * (p + 1) * lanes, six = round_up(6 * points * rs, 256);
   const bool curved = space->mesh->amplitude != 0.0;
-  op->scal_bytes = round_up(points * rs, 256);
-  op->tab_bytes = round_up(8 * (size_t)space->mesh->n * (p + 1) * sizeof(double), 256);
-  const size_t c64 = curved && op->precision == MFQ_FP32 && !op->mfma ? points * sizeof(double) : 0;
-  const size_t used = op->scal_bytes + op->tab_bytes + round_up(c64, 256);
-  const size_t six = round_up(6 * points * rs, 256);
-  op->has_c64 = c64 != 0;
-  op->full_bytes = op->mfma ? six : 0;
-  op->geo_bytes = curved && !op->mfma ? std::max(six, used) : used;
+  if (op->mfma) {
+    op->geo_bytes = six;
+  } else {
+    op->scal_bytes = round_up(points * rs, 256);
+    op->tab_bytes = round_up(8 * (size_t)space->mesh->n * (p + 1) * sizeof(double), 256);
+    op->has_c64 = curved && op->precision == MFQ_FP32;
+    op->geo_bytes = op->scal_bytes + op->tab_bytes + (op->has_c64 ? round_up(points * sizeof(double), 256) : 0);
+    if (curved) op->geo_bytes = std::max(op->geo_bytes, six);
+  }
   *out = op;
   return MFQ_OK;
 }
@@ -150,7 +151,7 @@ void mfq_op_destroy(mfq_op* op) { delete op; }
 
 int mfq_op_device_bytes(const mfq_op* op, size_t* bytes) {
   if (!op || !bytes) return fail(MFQ_EINVAL, "op or bytes is NULL");
-  *bytes = op->idx_bytes + op->geo_bytes + op->full_bytes;
+  *bytes = op->idx_bytes + op->geo_bytes;
   return MFQ_OK;
 }
 
@@ -172,15 +173,19 @@ int mfq_op_get_layout(const mfq_op* op, mfq_op_layout* out) {
 int mfq_op_bind(mfq_op* op, void* dev_buf, size_t bytes, void* hip_stream) {
   if (!op) return fail(MFQ_EINVAL, "op is NULL");
   if (!dev_buf || !aligned(dev_buf, 256)) return fail(MFQ_EINVAL, "buffer NULL or not 256-byte aligned");
-  const size_t need = op->idx_bytes + op->geo_bytes + op->full_bytes;
+  const size_t need = op->idx_bytes + op->geo_bytes;
   if (bytes < need) return fail(MFQ_ENOMEM, "buffer of %zu bytes, operator needs %zu", bytes, need);
   hipStream_t st = (hipStream_t)hip_stream;
   op->buf = dev_buf;
   op->idx = (int*)dev_buf;
-  op->scal = (char*)dev_buf + op->idx_bytes;
-  op->tab = (char*)op->scal + op->scal_bytes;
-  op->c64 = op->has_c64 ? (double*)((char*)op->tab + op->tab_bytes) : nullptr;
-  op->full = op->full_bytes ? (char*)op->scal + op->geo_bytes : nullptr;
+  char* const geo = (char*)dev_buf + op->idx_bytes;
+  if (op->mfma) {
+    op->full = geo;
+  } else {
+    op->scal = geo;
+    op->tab = geo + op->scal_bytes;
+    op->c64 = op->has_c64 ? (double*)(geo + op->scal_bytes + op->tab_bytes) : nullptr;
+  }
   const OpView v = view(op);
   const hipError_t e = launch_setup(v, op->precision, op->idx, op->tab, op->scal, op->c64, op->full, st);
   if (e != hipSuccess) {

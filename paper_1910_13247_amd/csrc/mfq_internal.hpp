@@ -164,7 +164,8 @@ struct mfq_op {
   bool mfma = false;          // FP32 cell loop on the matrix cores (created as MFQ_FP32_MFMA)
   bool fuse = MFQ_FUSE_DEFAULT != 0;  // vector updates fused into the cell loop (mfq_op_set_fused_updates)
   mfq::Bricks bricks;
-  size_t idx_bytes, scal_bytes, tab_bytes, geo_bytes, full_bytes;  // geo_bytes covers scal, tab and c64
+  size_t idx_bytes, geo_bytes;  // geo_bytes: all that follows the index lattices
+  size_t scal_bytes = 0, tab_bytes = 0;
   bool has_c64 = false;
   void* buf = nullptr;        // caller-owned device memory
   int* idx = nullptr;         // [n_bricks][lattice]: global node of each brick-lattice node,
