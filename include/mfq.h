@@ -149,8 +149,9 @@ int mfq_op_get_layout(const mfq_op* op, mfq_op_layout* out);
 /* diag = diagonal of A (1 on Dirichlet rows), computed matrix-free from the same quadrature. */
 int mfq_op_diagonal(const mfq_op* op, void* diag, void* hip_stream);
 
-/* Evaluates G (rounded to the operator's precision) into out as double [n_cells][(p+1)^3][6] in the order (xx, xy, xz, yy, yz, zz),
- * quadrature points lexicographic (x fastest).  For tests of the geometry precompute. */
+/* The tensor G that the operator applies, from the data it holds (c_q of its precision and the FP64
+ * tables, or the stored six values), into out as double [n_cells][(p+1)^3][6] in the order (xx, xy, xz,
+ * yy, yz, zz), quadrature points lexicographic (x fastest).  For tests of the geometry precompute. */
 int mfq_op_geometry(const mfq_op* op, double* out_device, void* hip_stream);
 
 /* b_i = sum_K sum_q f(x_q) phi_i(x_q) JxW_q (Sec. 2.4 right-hand-side term) for the manufactured
