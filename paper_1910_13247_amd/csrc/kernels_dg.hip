@@ -157,21 +157,29 @@ __device__ __forceinline__ void dg_line_terms(const Real (&u)[N1], const DgEnd<R
   }
 }
 
-// FP64: the scheduler does not carry work over this point (see dg_kron_kernel)
-template <typename Real>
+// Rules per degree and type, from times on MI355X in us (at the sizes given, without / with):
+// early: the lines beyond the row segment's ends are asked for with all others, not after the first barrier
+// (one memory latency less, the ends' registers and descriptors more).  FP64 Q3 50^3 39.2 / 38.5, Q4 40^3
+// 40.4 / 37.8, Q5 16^3 10.6 / 10.2 and 53^3 215 / 194, Q7 6^3 8.8 / 8.2 and 40^3 188 / 169, Q8 36^3 256 / 230;
+// not Q1 160^3 188 / 209, Q2 107^3 228 / 233, Q6 (spilled scalars) 14^3 12.6 / 14.2; FP32 Q4 40^3 27.4 / 25.8,
+// Q6 46^3 106 / 102, not Q8 36^3 110 / 119.
+constexpr bool dg_early(int p, bool fp64) { return fp64 ? p >= 3 && p != 6 : p <= 7; }
+// phases: the scheduler does not carry work over the points between the x and y terms (fewer registers;
+// FP64 Q5 33^3 43.7 / 40.0, Q7 40^3 193 / 169, but Q3 80^3 177 / 191, Q4 64^3 196 / 204, Q8 2^3 9.0 / 10.4).
+constexpr bool dg_phases(int p, bool fp64) { return fp64 && p >= 5 && p <= 7; }
+template <int P, typename Real>
 __device__ __forceinline__ void phase_end() {
-  if constexpr (sizeof(Real) == 8) __builtin_amdgcn_sched_barrier(0);
+  if constexpr (dg_phases(P, sizeof(Real) == 8)) __builtin_amdgcn_sched_barrier(0);
 }
 
 // What bounds it: LDS (95 accesses per lane at degree 4), vector arithmetic and the L1's line accesses at
-// similar shares, so the waves in flight decide.  Every global line but the row segment's ends is asked
-// for before the first barrier and reduced to the end value and derivative that are needed of it as it
-// arrives; in FP64 the x and y terms are kept apart, which leaves 82 registers at degree 4 (5 waves per
-// SIMD without spills; interleaved by the scheduler 102, and 4 waves).  The last contraction is along
-// z, where a lane's stores are contiguous across lanes.  Line after line per direction and the last
-// contraction along x: FP64 Q4 64^3 239 -> 218 us, Q7 32^3 109 -> 94, Q8 32^3 222 -> 192 (and 10.0 -> 11.1
-// at Q5 16^3, where one wave's chain counts); FP32 Q3 48^3 27 -> 23, Q8 32^3 91 -> 83.  EPI is an instance
-// of its own: as a branch it cost the plain operator 5 % (Q5 to Q8).
+// similar shares, so the waves in flight decide.  Every global line (dg_early: of the row segment's ends
+// too) is asked for before the first barrier and reduced to the end value and derivative that are needed
+// of it as it arrives.  The last contraction is along z, where a lane's stores are contiguous across
+// lanes.  Line after line per direction and the last contraction along x -> this: FP64 Q4 64^3 231 -> 196 us,
+// Q5 16^3 9.6 -> 10.2, Q6 14^3 11.3 -> 12.6 and 46^3 273 -> 234, Q7 40^3 246 -> 169, Q8 36^3 322 -> 224; FP32 Q3 80^3
+// 93 -> 81, Q8 36^3 124 -> 110.  EPI is an instance of its own: as a branch it cost the plain operator 5 % (Q5
+// to Q8).
 template <int P, typename Real, bool EPI>
 __global__ __launch_bounds__(DgCell<P>::THREADS) void dg_kron_kernel(const Real* __restrict__ src, int n, int slab_planes, Real h,
                                                                      Real sigma, DgKron<P, Real> kt, DgEpilogue<Real> ep) {
@@ -235,15 +243,31 @@ __global__ __launch_bounds__(DgCell<P>::THREADS) void dg_kron_kernel(const Real*
   for (int c = 0; c < N1; ++c) node_load(own, vz + T * B * c, 0, u[c]);
   const auto zLo = end(std::false_type{}, -nz, hasLo[2], vz, T * B), zHi = end(std::true_type{}, nz, hasHi[2], vz, T * B);
   const auto yLo = end(std::false_type{}, -ny, hasLo[1], vy, N1 * B), yHi = end(std::true_type{}, ny, hasHi[1], vy, N1 * B);
+  constexpr bool EARLY = dg_early(P, sizeof(Real) == 8);
+  DgEnd<Real> xLo, xHi;
+  if constexpr (EARLY) {
+    const int vx = live ? (lc * NQ + N1 * e) * B : kNoAccess;
+    xLo = end(std::false_type{}, -(int64_t)NQ, i0 > 0, lc == 0 ? vx : kNoAccess, B);
+    xHi = end(std::true_type{}, NQ, i0 + cnt < n, lc == cnt - 1 ? vx : kNoAccess, B);
+  }
 #pragma unroll
   for (int c = 0; c < N1; ++c) W1[oz + SZ * c] = u[c];
   Real wz[N1];
   dg_line_terms<N1>(u, zLo, zHi, hasLo[2], hasHi[2], h, ih, h2, sigma, kt, wz);
   __syncthreads();
   const int64_t gx = base + N1 * e;
-  const auto xLo = dg_end<N1, false, Real>(kt, [&](int a) { return lc > 0 ? W1[ox + a - R * T] : live && hasLo[0] ? src[gx - NQ + a] : (Real)0; });
-  const auto xHi = dg_end<N1, true, Real>(kt, [&](int a) { return lc + 1 < cnt ? W1[ox + a + R * T] : live && hasHi[0] ? src[gx + NQ + a] : (Real)0; });
-  phase_end<Real>();
+  const bool inLo = lc > 0, inHi = lc + 1 < cnt;  // the x-neighbour is in the row segment
+  const auto segLo = dg_end<N1, false, Real>(kt, [&](int a) {
+    if constexpr (EARLY) return W1[inLo ? ox + a - R * T : ox];
+    return inLo ? W1[ox + a - R * T] : live && hasLo[0] ? src[gx - NQ + a] : (Real)0;
+  });
+  const auto segHi = dg_end<N1, true, Real>(kt, [&](int a) {
+    if constexpr (EARLY) return W1[inHi ? ox + a + R * T : ox];
+    return inHi ? W1[ox + a + R * T] : live && hasHi[0] ? src[gx + NQ + a] : (Real)0;
+  });
+  if (!EARLY || inLo) xLo = segLo;
+  if (!EARLY || inHi) xHi = segHi;
+  phase_end<P, Real>();
   {
     Real w[N1];
 #pragma unroll
@@ -252,7 +276,7 @@ __global__ __launch_bounds__(DgCell<P>::THREADS) void dg_kron_kernel(const Real*
 #pragma unroll
     for (int a = 0; a < N1; ++a) W0[ox + a] = w[a];
   }
-  phase_end<Real>();
+  phase_end<P, Real>();
   Real wy[N1];
 #pragma unroll
   for (int b = 0; b < N1; ++b) u[b] = W1[oy + SY * b];
