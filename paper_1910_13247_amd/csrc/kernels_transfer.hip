@@ -16,7 +16,8 @@
 // Both stream columns of fine nodes along z through registers, coalesced along x, and do the x and y
 // passes in LDS on a tile of coarse cells.  A workgroup writes every node it owns once (its cells'
 // lower faces and interiors; the mesh's last cells also the upper faces): no atomics, no clearing, one
-// launch, a fixed summation order that does not depend on the tiling.
+// launch, a fixed summation order that does not depend on the tiling.  The restriction of the highest degrees
+// goes cell by cell where that is faster (Tile::by_cells).
 #include "batch.hpp"
 #include "kernels_common.hpp"
 
@@ -33,6 +34,19 @@ struct Tile {
   static constexpr int OX = S <= 2 ? 16 : S <= 4 ? 8 : S <= 6 ? 6 : S <= 8 ? 4 : S <= 10 ? 3 : S <= 14 ? 2 : 1;
   static constexpr int OY = S <= 2 ? 4 : S <= 4 ? 2 : 1;
   static constexpr int BLOCK = S >= 12 ? 512 : 256;
+  // The restriction's arrays leave one workgroup per CU in FP64 from degree 7 on, so it takes more lanes: a
+  // column of fine nodes each at degree 8 (16^3 -> 32^3 189 -> 155 us), two at degree 7 (14^3 96 -> 79).
+  template <typename Real>
+  static constexpr int rblock = sizeof(Real) == 8 && S >= 14 ? (S == 14 ? 640 : 1024) : BLOCK;
+  // Where the restriction goes cell by cell instead (restrict_cells), FP64 from degree 7 on: a single cell,
+  // where a tile's halo is most of the work (degree 7 12.4 -> 9.7 us, degree 8 14.2 -> 11.2), and large
+  // meshes, whose tiles read each fine node three to four times (degree 7 18^3 136 -> 127, 29^3 509 -> 408;
+  // degree 8 16^3 155 -> 155, 25^3 568 -> 539; below, degree 7 14^3 79 -> 89, 9^3 31 -> 67).  Batched transfers
+  // are FP32 and go by tiles.
+  template <typename Real>
+  static bool by_cells(int nc) {
+    return sizeof(Real) == 8 && S >= 14 && (nc == 1 || nc >= 17);
+  }
   static int tiles(int nc) { return ((nc + OX - 1) / OX) * ((nc + OY - 1) / OY); }
   // coarse layers that a workgroup of the restriction walks along z (the layer below its first one
   // is read once more): as many as leave a thousand workgroups
@@ -158,7 +172,7 @@ __device__ __forceinline__ void restrict_block(const Real* __restrict__ fine, co
                                                Real* __restrict__ coarse, int nc, int bc,
                                                int layers, const TransferTable<PC, NF1, Real>& tr, int b) {
   using T = Tile<PC, NF1>;
-  constexpr int M = PC + 1, S = T::S, BLOCK = T::BLOCK;
+  constexpr int M = PC + 1, S = T::S, BLOCK = T::template rblock<Real>;
   // fine nodes inside the cell below, the owned cells and, for the mesh's last vertex, their end
   constexpr int FX = (T::OX + 1) * S, FY = (T::OY + 1) * S;
   constexpr int WX = T::OX * PC + 1, WY = T::OY * PC + 1;
@@ -178,6 +192,11 @@ __device__ __forceinline__ void restrict_block(const Real* __restrict__ fine, co
     if constexpr (SUB) return fine[g] - minus[g];
     return fine[g];
   };
+  // the 1D matrix of the z pass: scalars, or from LDS at degree 7, where it would be spilled lane by lane
+  // and that costs more (FP64: 202 spilled scalars, 14^3 96 -> 84 us; FP32 45 -> 41; not at degree 8)
+  constexpr bool ZL = S == 14;
+  if (ZL) __syncthreads();
+  auto z = [&](int k) -> Real { return ZL ? Ps[k] : tr.P[k]; };
   // this thread's columns; fine nodes outside the mesh or in Dirichlet faces count as zero
   int64_t col[COLS];
   bool on[COLS];
@@ -193,7 +212,7 @@ __device__ __forceinline__ void restrict_block(const Real* __restrict__ fine, co
 #pragma unroll
       for (int i = 1; i < S; ++i) {
         const Real v = value(col[q] + plane * (S * (k0 - 1) + i));
-        carry[q] = fmad(tr.P[i * M + PC], on[q] ? v : (Real)0, carry[q]);
+        carry[q] = fmad(z(i * M + PC), on[q] ? v : (Real)0, carry[q]);
       }
     }
   }
@@ -237,8 +256,8 @@ __device__ __forceinline__ void restrict_block(const Real* __restrict__ fine, co
         for (int i = 1; i < S; ++i) {
           const Real v = on[q] ? fq[i] : (Real)0;
 #pragma unroll
-          for (int a = 0; a < PC; ++a) out[a] = fmad(tr.P[i * M + a], v, out[a]);
-          carry[q] = fmad(tr.P[i * M + PC], v, carry[q]);
+          for (int a = 0; a < PC; ++a) out[a] = fmad(z(i * M + a), v, out[a]);
+          carry[q] = fmad(z(i * M + PC), v, carry[q]);
         }
       }
       if (sizeof(Real) == 4) out[0] += end;
@@ -270,10 +289,80 @@ __device__ __forceinline__ void restrict_block(const Real* __restrict__ fine, co
 }
 
 template <int PC, int NF1, typename Real, bool SUB>
-__global__ __launch_bounds__((Tile<PC, NF1>::BLOCK)) void restrict_kernel(const Real* __restrict__ fine,
+__global__ __launch_bounds__((Tile<PC, NF1>::template rblock<Real>)) void restrict_kernel(const Real* __restrict__ fine,
                                                                         const Real* __restrict__ minus,
                                                                         Real* __restrict__ coarse, int nc, int bc, int layers, TransferTable<PC, NF1, Real> tr) {
   restrict_block<PC, NF1, Real, SUB>(fine, minus, coarse, nc, bc, layers, tr, (int)blockIdx.x);
+}
+
+// Restriction cell by cell: coarse cell b of colour `colour` by the workgroup.  Fine values are weighted by 1 /
+// (number of coarse cells that hold the node), so the cells' transposes sum to P^T; cells of one colour
+// (parities of the coordinates) share no coarse node and add with plain stores, colours in order, into the
+// cleared coarse vector.
+constexpr int kCellBlock = 512;
+template <int PC, int NF1, typename Real, bool SUB>
+__global__ __launch_bounds__(kCellBlock) void restrict_cells_kernel(const Real* __restrict__ fine, const Real* __restrict__ minus,
+                                                                   Real* __restrict__ coarse, int nc, int bc, int colour,
+                                                                   TransferTable<PC, NF1, Real> tr) {
+  constexpr int M = PC + 1, S = NF1 - 1;
+  __shared__ Real f[NF1 * NF1 * NF1];  // the cell's fine nodes, zero on Dirichlet nodes
+  __shared__ Real t1[M * NF1 * NF1];   // after x: [l][j][a]
+  __shared__ Real t2[M * M * NF1];     // after y: [l][b][a]
+  __shared__ Real Ps[NF1 * M];
+  const int px = colour & 1, py = (colour >> 1) & 1, pz = colour >> 2;
+  const int cxn = (nc + 1 - px) / 2, cyn = (nc + 1 - py) / 2, b = (int)blockIdx.x;
+  const int ic = 2 * (b % cxn) + px, jc = 2 * (b / cxn % cyn) + py, kc = 2 * (b / (cxn * cyn)) + pz;
+  const int E = PC * nc, Ef = S * nc;
+  const int64_t N1c = E + 1, N1f = Ef + 1;
+  auto share = [&](int i, int cell) -> Real { return (i == 0 && cell > 0) || (i == S && cell < nc - 1) ? (Real)0.5 : (Real)1; };
+  for (int k = threadIdx.x; k < NF1 * M; k += kCellBlock) Ps[k] = tr.P[k];
+  for (int k = threadIdx.x; k < NF1 * NF1 * NF1; k += kCellBlock) {
+    const int I = S * ic + k % NF1, J = S * jc + k / NF1 % NF1, K = S * kc + k / (NF1 * NF1);
+    const bool zero = bc && (I == 0 || J == 0 || K == 0 || I == Ef || J == Ef || K == Ef);
+    const int64_t g = I + N1f * (J + N1f * K);
+    Real v = fine[g];
+    if constexpr (SUB) v -= minus[g];
+    f[k] = zero ? (Real)0 : v;
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < M * NF1 * NF1; k += kCellBlock) {
+    const int a = k % M, j = k / M % NF1, l = k / (M * NF1);
+    Real s = 0;
+#pragma unroll
+    for (int i = 0; i < NF1; ++i) s = fmad(Ps[i * M + a] * share(i, ic), f[i + NF1 * (j + NF1 * l)], s);
+    t1[k] = s * (share(j, jc) * share(l, kc));
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < M * M * NF1; k += kCellBlock) {
+    const int a = k % M, bb = k / M % M, l = k / (M * M);
+    Real s = 0;
+#pragma unroll
+    for (int j = 0; j < NF1; ++j) s = fmad(Ps[j * M + bb], t1[a + M * (j + NF1 * l)], s);
+    t2[k] = s;
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < M * M * M; k += kCellBlock) {
+    const int a = k % M, bb = k / M % M, c = k / (M * M);
+    Real s = 0;
+#pragma unroll
+    for (int l = 0; l < NF1; ++l) s = fmad(Ps[l * M + c], t2[a + M * (bb + M * l)], s);
+    const int I = PC * ic + a, J = PC * jc + bb, K = PC * kc + c;
+    const bool bnd = bc && (I == 0 || J == 0 || K == 0 || I == E || J == E || K == E);
+    if (!bnd) coarse[I + N1c * (J + N1c * K)] += s;
+  }
+}
+
+template <int PC, int NF1, typename Real, bool SUB>
+hipError_t restrict_cells(const Real* fine, const Real* minus, Real* coarse, int64_t n_coarse, int nc, int bc,
+                          const TransferTable<PC, NF1, Real>& tr, hipStream_t st) {
+  hipError_t e = launch_fill(sizeof(Real) == 8 ? MFQ_FP64 : MFQ_FP32, coarse, n_coarse, 0.0, st);
+  if (e != hipSuccess) return e;
+  for (int c = 0; c < kColours; ++c) {
+    const int64_t cells = (int64_t)((nc + 1 - (c & 1)) / 2) * ((nc + 1 - ((c >> 1) & 1)) / 2) * ((nc + 1 - (c >> 2)) / 2);
+    if (cells == 0) continue;
+    restrict_cells_kernel<PC, NF1, Real, SUB><<<(unsigned)cells, kCellBlock, 0, st>>>(fine, minus, coarse, nc, bc, c, tr);
+  }
+  return hipGetLastError();
 }
 
 // Batched forms (serving): workgroup b belongs to the item whose range [first, next first) holds it and
@@ -337,10 +426,19 @@ hipError_t transfer_pnr(const mfq_transfer* t, TransferOp op, const Real* in, co
     prolongate_kernel<PC, NF1, Real, false><<<grid, T::BLOCK, 0, st>>>(in, out, nc, bc, tr);
   else if (op == kProlongateAdd)
     prolongate_kernel<PC, NF1, Real, true><<<grid, T::BLOCK, 0, st>>>(in, out, nc, bc, tr);
-  else if (op == kRestrict)
-    restrict_kernel<PC, NF1, Real, false><<<grid, T::BLOCK, 0, st>>>(in, nullptr, out, nc, bc, T::layers(nc), tr);
-  else
-    restrict_kernel<PC, NF1, Real, true><<<grid, T::BLOCK, 0, st>>>(in, minus, out, nc, bc, T::layers(nc), tr);
+  else {
+    constexpr int RB = T::template rblock<Real>;
+    if constexpr (sizeof(Real) == 8 && T::S >= 14)
+      if (T::template by_cells<Real>(nc)) {
+        const int64_t n = t->coarse->n_dofs;
+        return op == kRestrict ? restrict_cells<PC, NF1, Real, false>(in, nullptr, out, n, nc, bc, tr, st)
+                               : restrict_cells<PC, NF1, Real, true>(in, minus, out, n, nc, bc, tr, st);
+      }
+    if (op == kRestrict)
+      restrict_kernel<PC, NF1, Real, false><<<grid, RB, 0, st>>>(in, nullptr, out, nc, bc, T::layers(nc), tr);
+    else
+      restrict_kernel<PC, NF1, Real, true><<<grid, RB, 0, st>>>(in, minus, out, nc, bc, T::layers(nc), tr);
+  }
   return hipGetLastError();
 }
 
