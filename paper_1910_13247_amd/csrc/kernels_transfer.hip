@@ -152,16 +152,16 @@ __device__ __forceinline__ Real restrict_node(const Real* f, int st, int o, int 
   constexpr int M = PC + 1, S = NF1 - 1;
   const int cell = o / PC, a = o - cell * PC;
   const Real* v = f + (S * (cell + 1) - 1) * st;
-  Real s = 0;
+  Real lo = 0, hi = 0;
   if (a == 0) {
 #pragma unroll
-    for (int i = 1; i < S; ++i) s = fmad(Ps[i * M + PC], v[(i - S) * st], s);
+    for (int i = 1; i < S; ++i) lo = fmad(Ps[i * M + PC], v[(i - S) * st], lo);
   }
   if (cell < cells) {
 #pragma unroll
-    for (int i = 1; i < S; ++i) s = fmad(Ps[i * M + a], v[i * st], s);
+    for (int i = S - 1; i > 0; --i) hi = fmad(Ps[i * M + a], v[i * st], hi);
   }
-  return a == 0 ? s + v[0] : s;  // the largest term last
+  return a == 0 ? lo + hi + v[0] : hi;  // each cell's terms towards the vertex, its own (the largest) last
 }
 
 // restriction of `fine`, or with SUB of fine - minus (the multigrid residual b - A x, which is then
@@ -192,9 +192,9 @@ __device__ __forceinline__ void restrict_block(const Real* __restrict__ fine, co
     if constexpr (SUB) return fine[g] - minus[g];
     return fine[g];
   };
-  // the 1D matrix of the z pass: scalars, or from LDS at degree 7, where it would be spilled lane by lane
-  // and that costs more (FP64: 202 spilled scalars, 14^3 96 -> 84 us; FP32 45 -> 41; not at degree 8)
-  constexpr bool ZL = S == 14;
+  // the 1D matrix of the z pass: scalars, or from LDS at degree 7 in FP64, where it would be spilled lane by lane
+  // and that costs more (FP64: 202 spilled scalars, 14^3 96 -> 84 us; not at degree 8, and FP32 29^3 274 -> 290)
+  constexpr bool ZL = S == 14 && sizeof(Real) == 8;
   if (ZL) __syncthreads();
   auto z = [&](int k) -> Real { return ZL ? Ps[k] : tr.P[k]; };
   // this thread's columns; fine nodes outside the mesh or in Dirichlet faces count as zero
@@ -245,9 +245,12 @@ __device__ __forceinline__ void restrict_block(const Real* __restrict__ fine, co
       Real(&fq)[S] = f[AHEAD ? q : 0];
       if constexpr (!AHEAD) load(kc, q, fq);
       Real out[PC];
-      // (rounding: FP32 adds the largest term last, FP64 frees its register first)
+      // (rounding: FP32 as restrict_node, but for the order of the terms where the matrix's scalars are
+      // spilled and a second walk through them costs a tenth; FP64 frees registers first)
+      constexpr bool DOWN = sizeof(Real) == 4 && S < 14;
       const Real end = on[q] && !bz ? fq[0] : (Real)0;
-      out[0] = sizeof(Real) == 8 ? carry[q] + end : carry[q];
+      const Real below = carry[q];
+      out[0] = sizeof(Real) == 8 ? below + end : (Real)0;
       if (!last) {
 #pragma unroll
         for (int a = 1; a < PC; ++a) out[a] = 0;
@@ -256,11 +259,15 @@ __device__ __forceinline__ void restrict_block(const Real* __restrict__ fine, co
         for (int i = 1; i < S; ++i) {
           const Real v = on[q] ? fq[i] : (Real)0;
 #pragma unroll
-          for (int a = 0; a < PC; ++a) out[a] = fmad(z(i * M + a), v, out[a]);
+          for (int a = DOWN; a < PC; ++a) out[a] = fmad(z(i * M + a), v, out[a]);
           carry[q] = fmad(z(i * M + PC), v, carry[q]);
         }
+        if (DOWN) {
+#pragma unroll
+          for (int i = S - 1; i > 0; --i) out[0] = fmad(z(i * M), on[q] ? fq[i] : (Real)0, out[0]);
+        }
       }
-      if (sizeof(Real) == 4) out[0] += end;
+      if (sizeof(Real) == 4) out[0] = below + out[0] + end;
       if (k < FX * FY) {
         const int x = k % FX, y = k / FX;
         if (last)
