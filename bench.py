@@ -104,18 +104,17 @@ def hierarchy(p, n, limit=4096):
     return lv[::-1]
 
 
-def geo_saving(p, n, b, cart=False, coef=False):
+def geo_saving(p, n, b, cart=False):
     """Bytes an operator application does not read: the value per point on undeformed cells with
     coefficient 1 (with a variable coefficient it is read, as on curved cells)."""
     return (1 if cart else 0) * b * n ** 3 * (p + 1) ** 3
 
 
-def vcycle_bytes(levels, b, smoother_degree=3, coarse_mode=0, coarse_degree=16, cart=False, coef=False):
+def vcycle_bytes(levels, b, smoother_degree=3, coarse_mode=0, coarse_degree=16, cart=False):
     """Algorithmic bytes of one V-cycle over `levels` (coarsest first) in value size b."""
     N = [(p_ * n_ + 1) ** 3 for p_, n_ in levels]
     k = smoother_degree
-    op = lambda l: algorithmic_bytes(levels[l][0], levels[l][1], b) - geo_saving(levels[l][0], levels[l][1], b,
-                                                                                  cart, coef)
+    op = lambda l: algorithmic_bytes(levels[l][0], levels[l][1], b) - geo_saving(levels[l][0], levels[l][1], b, cart)
     tot = 0
     for l in range(1, len(levels)):
         streams = 5 + 8 * (k - 1) + 3 + 3 + 7 + 8 * (k - 1)
@@ -129,28 +128,27 @@ def vcycle_bytes(levels, b, smoother_degree=3, coarse_mode=0, coarse_degree=16, 
     return tot
 
 
-def solve_bytes(kind, p, n, iterations, passes, smoother_degree=3, coarse_mode=0, coarse_degree=16, cart=False,
-                coef=False):
+def solve_bytes(kind, p, n, iterations, passes, smoother_degree=3, coarse_mode=0, coarse_degree=16, cart=False):
     """Algorithmic bytes of a whole solve (iterations summed over passes, `passes` residual checks)."""
     N = (p * n + 1) ** 3
-    op64 = algorithmic_bytes(p, n, 8) - geo_saving(p, n, 8, cart, coef)
+    op64 = algorithmic_bytes(p, n, 8) - geo_saving(p, n, 8, cart)
     check = op64 + 3 * 8 * N
     if kind == "cg_fp64":
         return iterations * (op64 + 11 * 8 * N) + passes * check
     lv = hierarchy(p, n)
     if kind == "gmg_fp64":
-        vc = vcycle_bytes(lv, 8, smoother_degree, coarse_mode, coarse_degree, cart, coef)
+        vc = vcycle_bytes(lv, 8, smoother_degree, coarse_mode, coarse_degree, cart)
         return iterations * (op64 + 13 * 8 * N + vc) + passes * check
-    vc = vcycle_bytes(lv, 4, smoother_degree, coarse_mode, coarse_degree, cart, coef) + 24 * N
+    vc = vcycle_bytes(lv, 4, smoother_degree, coarse_mode, coarse_degree, cart) + 24 * N
     if kind == "gmg_mixed":
         return iterations * (op64 + 13 * 8 * N + vc) + passes * check
     # gmg_mixed_ir: inner CG on the FP32 operator (casts p in and Ap out: 24 B per DoF) with FP64
     # vectors; each pass also adds its correction into x (3 x 8 N)
-    op32 = algorithmic_bytes(p, n, 4) - geo_saving(p, n, 4, cart, coef)
+    op32 = algorithmic_bytes(p, n, 4) - geo_saving(p, n, 4, cart)
     return iterations * (op32 + 24 * N + 13 * 8 * N + vc) + passes * (check + 3 * 8 * N)
 
 
-def setup_bytes(p, n, smoother_degree=3, coarse_mode=1, lanczos=12, coef=False):
+def setup_bytes(p, n, smoother_degree=3, coarse_mode=1, lanczos=12):
     """Algorithmic bytes of a solver's set-up on the device: index maps and the value per point
     written for the FP64 operator and every FP32 level, each level's diagonal (both read, diagonal
     written), and the Lanczos steps (operator + about 10 vector streams each)."""
@@ -161,7 +159,7 @@ def setup_bytes(p, n, smoother_degree=3, coarse_mode=1, lanczos=12, coef=False):
         geo4 = 8 * nl ** 3 * (pl + 1) ** 3                      # idx + value in FP32
         tot += geo4 + geo4 + 4 * Nl                             # written, read back by the diagonal
         if l > 0 or coarse_mode == 1:
-            tot += lanczos * (algorithmic_bytes(pl, nl, 4) - geo_saving(pl, nl, 4, coef=coef) + 10 * 4 * Nl)
+            tot += lanczos * (algorithmic_bytes(pl, nl, 4) - geo_saving(pl, nl, 4) + 10 * 4 * Nl)
     return tot + 12 * n ** 3 * (p + 1) ** 3                     # FP64 operator's idx + value written
 
 
@@ -638,8 +636,8 @@ def serve_benchmark(n_requests, rate=200.0, seed=0, iters_per_step=2, n_streams=
     kw = dict(smoother_degree=prm.get("smoother_degree", 3), coarse_mode=prm.get("coarse_mode", 1),
               coarse_degree=prm.get("coarse_degree", 16))
     lz = prm.get("lanczos_iters", srv.ex.params.get("lanczos_iters", 12))
-    tot = sum(solve_bytes("gmg_mixed", r.degree, r.n, r.iterations, 1, cart=r.alpha == 0, coef=r.alpha != 0, **kw) +
-              setup_bytes(r.degree, r.n, kw["smoother_degree"], kw["coarse_mode"], lz, coef=r.alpha != 0)
+    tot = sum(solve_bytes("gmg_mixed", r.degree, r.n, r.iterations, 1, cart=r.alpha == 0, **kw) +
+              setup_bytes(r.degree, r.n, kw["smoother_degree"], kw["coarse_mode"], lz)
               for r in srv.done)
     st["algorithmic_bytes"] = tot
     st["aggregate_algorithmic_GBs"] = tot / st["wall_s"] / 1e9

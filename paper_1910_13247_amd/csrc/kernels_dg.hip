@@ -451,42 +451,42 @@ __global__ __launch_bounds__(256) void dg_diag_kernel(Real* __restrict__ diag, i
 // Continuous Q_p (lattice of (pn+1)^3 nodes, Dirichlet nodes zero) <-> DG on the same mesh and
 // nodes.  Prolongation copies each lattice node into every cell that holds it; restriction (its
 // transpose) sums, per free lattice node, the entries of the cells that hold it in a fixed order.
-// The switch kernels are HBM bound once their index arithmetic is: degree known at compile time and, below
-// 2^31 entries, 32-bit indices (64-bit divisions by run-time sizes took as long as the accesses).  ADD: dg += E cg.
+// The switch kernels are HBM bound once their index arithmetic is: degree known at compile time and 32-bit
+// indices (a DG space has less than 2^31 entries; 64-bit divisions by run-time sizes took as long as the
+// accesses).  ADD: dg += E cg.
 // Q4 80^3 FP32: E 265 us and the addition after it 76, now 196 together; E^T 230 -> 208.
-template <int P, typename Real, typename IT, bool ADD>
+template <int P, typename Real, bool ADD>
 __global__ __launch_bounds__(256) void dg_from_cg_kernel(const Real* __restrict__ cg, Real* __restrict__ dg, int n) {
   constexpr unsigned N1 = P + 1, NL = N1 * N1 * N1;
-  const IT nc = (IT)n, L1 = P * nc + 1, N = nc * nc * nc * NL, step = (IT)gridDim.x * 256;
-  for (IT g = (IT)blockIdx.x * 256 + threadIdx.x; g < N; g += step) {
-    const IT K = g / NL, row = K / nc, plane = row / nc;
-    const unsigned i = (unsigned)(g - K * NL);
-    const IT I = P * (K - row * nc) + i % N1, J = P * (row - plane * nc) + i / N1 % N1, L = P * plane + i / (N1 * N1);
+  const unsigned nc = (unsigned)n, L1 = P * nc + 1, N = nc * nc * nc * NL, step = gridDim.x * 256;
+  for (unsigned g = blockIdx.x * 256 + threadIdx.x; g < N; g += step) {
+    const unsigned K = g / NL, row = K / nc, plane = row / nc;
+    const unsigned i = g - K * NL;
+    const unsigned I = P * (K - row * nc) + i % N1, J = P * (row - plane * nc) + i / N1 % N1, L = P * plane + i / (N1 * N1);
     const Real v = cg[I + L1 * (J + L1 * L)];
     dg[g] = ADD ? dg[g] + v : v;
   }
 }
 
 // per node the sum of its cell copies, lower cell first in every direction; zero on the boundary
-template <int P, typename Real, typename IT>
+template <int P, typename Real>
 __global__ __launch_bounds__(256) void cg_from_dg_kernel(const Real* __restrict__ dg, Real* __restrict__ cg, int n) {
   constexpr unsigned N1 = P + 1, NL = N1 * N1 * N1;
-  const IT nc = (IT)n, pn = P * nc, L1 = pn + 1, M = L1 * L1 * L1, step = (IT)gridDim.x * 256;
-  for (IT g = (IT)blockIdx.x * 256 + threadIdx.x; g < M; g += step) {
-    const IT row = g / L1, plane = row / L1;
-    const IT X[3] = {g - row * L1, row - plane * L1, plane};
+  const unsigned nc = (unsigned)n, pn = P * nc, L1 = pn + 1, M = L1 * L1 * L1, step = gridDim.x * 256;
+  for (unsigned g = blockIdx.x * 256 + threadIdx.x; g < M; g += step) {
+    const unsigned row = g / L1, plane = row / L1;
+    const unsigned X[3] = {g - row * L1, row - plane * L1, plane};
     if (X[0] == 0 || X[0] == pn || X[1] == 0 || X[1] == pn || X[2] == 0 || X[2] == pn) {
       cg[g] = (Real)0;
       continue;
     }
     // per direction the first cell that holds the node, the node's place there, and whether the next
     // cell holds it too (a cell vertex)
-    IT c[3];
-    unsigned a[3], two[3];
+    unsigned c[3], a[3], two[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       c[d] = X[d] / P;
-      a[d] = (unsigned)(X[d] - P * c[d]);
+      a[d] = X[d] - P * c[d];
       two[d] = a[d] == 0;
       if (two[d]) {
         c[d] -= 1;
@@ -497,7 +497,7 @@ __global__ __launch_bounds__(256) void cg_from_dg_kernel(const Real* __restrict_
     for (unsigned kz = 0; kz <= two[2]; ++kz)
       for (unsigned ky = 0; ky <= two[1]; ++ky)
         for (unsigned kx = 0; kx <= two[0]; ++kx) {
-          const IT K = c[0] + kx + nc * (c[1] + ky + nc * (c[2] + kz));
+          const unsigned K = c[0] + kx + nc * (c[1] + ky + nc * (c[2] + kz));
           s += dg[K * NL + (kx ? 0 : a[0]) + N1 * ((ky ? 0 : a[1]) + N1 * (kz ? 0 : a[2]))];
         }
     cg[g] = s;
@@ -562,24 +562,22 @@ hipError_t launch_dg_diagonal(int p, int n, int precision, void* diag, hipStream
 }
 
 namespace {
-template <int P, typename Real, typename IT>
-void dg_transfer_pr(int n, int64_t N, DgSwitch op, const void* in, void* out, hipStream_t st) {
-  const int64_t L1 = (int64_t)P * n + 1;
+template <int P, typename Real>
+void dg_transfer_pr(int n, DgSwitch op, const void* in, void* out, hipStream_t st) {
+  const int64_t N = (int64_t)n * n * n * (P + 1) * (P + 1) * (P + 1), L1 = (int64_t)P * n + 1;
   if (op == kDgFromCg)
-    dg_from_cg_kernel<P, Real, IT, false><<<dg_grid(N), 256, 0, st>>>((const Real*)in, (Real*)out, n);
+    dg_from_cg_kernel<P, Real, false><<<dg_grid(N), 256, 0, st>>>((const Real*)in, (Real*)out, n);
   else if (op == kDgAddFromCg)
-    dg_from_cg_kernel<P, Real, IT, true><<<dg_grid(N), 256, 0, st>>>((const Real*)in, (Real*)out, n);
+    dg_from_cg_kernel<P, Real, true><<<dg_grid(N), 256, 0, st>>>((const Real*)in, (Real*)out, n);
   else
-    cg_from_dg_kernel<P, Real, IT><<<dg_grid(L1 * L1 * L1), 256, 0, st>>>((const Real*)in, (Real*)out, n);
+    cg_from_dg_kernel<P, Real><<<dg_grid(L1 * L1 * L1), 256, 0, st>>>((const Real*)in, (Real*)out, n);
 }
 template <int P>
 hipError_t dg_transfer_p(int n, int precision, DgSwitch op, const void* in, void* out, hipStream_t st) {
-  const int64_t N = (int64_t)n * n * n * (P + 1) * (P + 1) * (P + 1);
-  const bool small = N <= 0x7fffffff;  // (the lattice has no more nodes than that)
   if (precision == MFQ_FP64)
-    small ? dg_transfer_pr<P, double, unsigned>(n, N, op, in, out, st) : dg_transfer_pr<P, double, int64_t>(n, N, op, in, out, st);
+    dg_transfer_pr<P, double>(n, op, in, out, st);
   else
-    small ? dg_transfer_pr<P, float, unsigned>(n, N, op, in, out, st) : dg_transfer_pr<P, float, int64_t>(n, N, op, in, out, st);
+    dg_transfer_pr<P, float>(n, op, in, out, st);
   return hipGetLastError();
 }
 }  // namespace

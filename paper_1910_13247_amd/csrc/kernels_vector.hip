@@ -368,10 +368,8 @@ __global__ __launch_bounds__(kVBlock) void residual_norm_kernel(const double* __
 }
 
 // x += c
-template <typename Real, typename Cor>
-__global__ __launch_bounds__(kVBlock) void add_kernel(Real* __restrict__ x, const Cor* __restrict__ c, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)kVBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kVBlock)
-    x[i] += (Real)c[i];
+__global__ __launch_bounds__(kVBlock) void add_kernel(double* __restrict__ x, const double* __restrict__ c, int64_t n) {
+  for (int64_t i = blockIdx.x * (int64_t)kVBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kVBlock) x[i] += c[i];
 }
 
 // ---------------------------------------------------------------- Chebyshev smoother
@@ -836,16 +834,8 @@ hipError_t launch_residual_norm(const double* b, const double* t, double* r, int
   residual_norm_kernel<<<vgrid(n), kVBlock, 0, st>>>(b, t, r, n, s, out);
   return hipGetLastError();
 }
-hipError_t launch_add(int precision, void* x, int cor_precision, const void* c, int64_t n, hipStream_t st) {
-  const int g = vgrid(n) * 4;
-  if (precision == MFQ_FP64 && cor_precision == MFQ_FP64)
-    add_kernel<double, double><<<g, kVBlock, 0, st>>>((double*)x, (const double*)c, n);
-  else if (precision == MFQ_FP64 && cor_precision == MFQ_FP32)
-    add_kernel<double, float><<<g, kVBlock, 0, st>>>((double*)x, (const float*)c, n);
-  else if (precision == MFQ_FP32 && cor_precision == MFQ_FP32)
-    add_kernel<float, float><<<g, kVBlock, 0, st>>>((float*)x, (const float*)c, n);
-  else
-    return hipErrorInvalidValue;
+hipError_t launch_add(double* x, const double* c, int64_t n, hipStream_t st) {
+  add_kernel<<<vgrid(n) * 4, kVBlock, 0, st>>>(x, c, n);
   return hipGetLastError();
 }
 hipError_t launch_cheb_first(int precision, const void* b, const void* t, const void* dinv, void* x, void* r, void* d,

@@ -314,7 +314,7 @@ hipError_t launch_cg_small(double* x, double* r, double* p, const double* Ap, co
                            hipStream_t st);
 hipError_t launch_residual_norm(const double* b, const double* t, double* r, int64_t n, SolverState* s, double* out,
                                 hipStream_t st);
-hipError_t launch_add(int precision, void* x, int cor_precision, const void* c, int64_t n, hipStream_t st);
+hipError_t launch_add(double* x, const double* c, int64_t n, hipStream_t st);
 hipError_t launch_cheb_first(int precision, const void* b, const void* t, const void* dinv, void* x, void* r, void* d,
                              int64_t n, double inv_theta, bool x_is_zero, hipStream_t st);
 hipError_t launch_cheb_step(int precision, const void* Ad, const void* dinv, void* x, void* r, void* d, int64_t n,

@@ -599,7 +599,7 @@ int step_enqueue(mfq_solver* s, int iters) {
     R.enqueued += m;
     MFQ_HIP(hipMemcpyAsync(&s->hstat->head, s->state, offsetof(SolverState, partials), hipMemcpyDeviceToHost, R.st));
   } else if (R.phase == Run::kCheck) {
-    if (R.sol != R.x) MFQ_HIP(launch_add(MFQ_FP64, R.x, MFQ_FP64, R.sol, N, R.st));
+    if (R.sol != R.x) MFQ_HIP(launch_add(R.x, R.sol, N, R.st));
     if (int rc = op_vmult(s->op64, R.x, s->Ap, R.st)) return rc;
     MFQ_HIP(launch_residual_norm(R.b, s->Ap, s->rout, N, s->aux, s->scal, R.st));
     MFQ_HIP(hipMemcpyAsync(&s->hstat->cert, s->scal, 8, hipMemcpyDeviceToHost, R.st));
@@ -2228,7 +2228,7 @@ int mfq_dg_solve(mfq_dg_solver* s, const double* b, double* x, double rtol, int 
     if (int rc = pcg(A, &M, nullptr, s->kres, s->kc, s->kr, s->kp, s->kAp, s->kz, s->N, s->state, tol, max_iter - iters,
                      s->prm.check_every, st, rc2))
       return rc;
-    MFQ_HIP(launch_add(MFQ_FP64, x, MFQ_FP64, s->kc, s->N, st));
+    MFQ_HIP(launch_add(x, s->kc, s->N, st));
     iters += rc2.iters;
     ++passes;
   }
