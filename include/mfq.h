@@ -115,8 +115,9 @@ int mfq_space_random(const mfq_space* space, int precision, void* x, uint64_t se
  * a(x_q) det(J_q) J_q^{-1} J_q^{-T} follows from them exactly: the map's Jacobian is I + 1 g^T with g
  * a product of 1D functions, so G_q = c_q (D^2 I - D (1 g^T + g 1^T) + |g|^2 1 1^T), D = 1 + g1 + g2
  * + g3, c_q = w_q a(x_q) h / D (evaluated in FP64, rounded once); g and D are held and applied in FP64.
- * MFQ_FP32_MFMA operators store the six values of G_q as well.  On deformed meshes the reported size is that of six values per
- * point, of which the first sixth is used. */
+ * MFQ_FP32_MFMA operators store the six values of G_q instead of c_q and the tables.  On deformed meshes
+ * the reported size is that of six values per point, of which FP64 operators use the first sixth and FP32
+ * operators the first half (c_q in FP32 and, for the diagonal, in FP64). */
 int mfq_op_create(const mfq_space* space, double alpha, int precision, mfq_op** out);
 void mfq_op_destroy(mfq_op* op);
 int mfq_op_device_bytes(const mfq_op* op, size_t* bytes);

@@ -1,5 +1,5 @@
 """The operator's coloured form, on meshes above the sizes at which the one-launch form takes over
-(FP64: 67, 45, 31, 22, 21, 13, 12, 11 cells per direction for p = 1..8; FP32: 79, 49, 40, 25, 21, 15, 14,
+(FP64: 67, 45, 31, 22, 19, 13, 11, 11 cells per direction for p = 1..8; FP32: 79, 49, 40, 23, 21, 15, 14,
 11), with a ragged last brick along x, in every geometry form, both precisions, overwriting and accumulating."""
 import itertools
 
